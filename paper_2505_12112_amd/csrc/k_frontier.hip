@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "lookback.h"
 
 namespace rp {
 
@@ -179,11 +180,6 @@ __global__ void k_corr_mark(int agg, LayerPtrs lp, Adj out, Adj in, const int *i
   }
 }
 
-// Per-tile sums carried by the compaction: marked vertices, their out-degrees,
-// their in-degrees, marked vertices of the first bitmap, and in the bucket form (NV
-// = kVals, else one fewer) their bucket counts.
-constexpr int kVals = 5;
-
 // Exclusive block scan of NV values at once (one LDS round; the caller's next
 // barrier frees lds).
 template <int NV>
@@ -223,31 +219,19 @@ __device__ inline void block_scan(const long long (&v)[NV], long long (&excl)[NV
   }
 }
 
-// Published tile sums: each 64-bit word holds the launch epoch (1..65535) above a
-// 48-bit value, so a word is valid on its own and words of earlier launches are
-// never mistaken for current ones (the tiles of every launch rewrite all words).
-constexpr int kEpochShift = 48;
-constexpr u64 kValueMask = (1ull << kEpochShift) - 1;
 constexpr int kSpinLimit = 1 << 20;
 
+// A tile's sums to and from its words (see lookback.h).
 template <int NV>
 __device__ inline void publish(u64 *p, u64 epoch, const long long (&v)[NV]) {
-#pragma unroll
-  for (int k = 0; k < NV; ++k)
-    __hip_atomic_store(p + k, epoch << kEpochShift | (static_cast<u64>(v[k]) & kValueMask), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+  publish_words(epoch, v,
+                [p](int k, u64 w) { __hip_atomic_store(p + k, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); });
 }
 
 template <int NV>
 __device__ inline bool fetch(const u64 *p, u64 epoch, long long (&v)[NV]) {
-  bool ok = true;
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const u64 w = __hip_atomic_load(p + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    ok = ok && (w >> kEpochShift) == epoch;
-    v[k] = static_cast<long long>(w & kValueMask);
-  }
-  return ok;
+  return fetch_words(epoch, v,
+                     [p](int k) { return __hip_atomic_load(p + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); });
 }
 
 // V consecutive values from p (16-byte aligned), zeros past `left` of them.
@@ -380,7 +364,7 @@ __global__ __launch_bounds__(kCompactThreads, 3) void k_compact(unsigned *bm_a, 
   // The ticket counter only grows and every launch on this scratch has the same
   // number of blocks, each taking one ticket, so launch k holds tickets k * tiles
   // .. k * tiles + tiles - 1: the ticket's quotient names the launch.
-  if (tid == 0) epoch_s = ticket_no / static_cast<u64>(tiles) % 65535 + 1;
+  if (tid == 0) epoch_s = launch_epoch(ticket_no, static_cast<u64>(tiles));
   long long ex[NV], tot[NV];
   block_scan(st, ex, tot, red);  // its barrier also publishes epoch_s
   const u64 epoch = epoch_s;
