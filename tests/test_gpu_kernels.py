@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2505_12112_amd import synth
+from paper_2505_12112_amd.ripple import Ripple
 from tests.harness import Pair, check_embeddings_conditioned, fp32_forward_bound, random_valid_batch
 
 pytestmark = pytest.mark.gpu
@@ -203,3 +204,46 @@ def test_reads_of_every_size(count):
         np.testing.assert_array_equal(p.lib.get_aggregates(1, ids), p.lib.get_aggregates(1)[ids])
     finally:
         p.close()
+
+
+class _OneLayer:
+    """A one-layer GraphConv-sum model without a bias."""
+
+    def __init__(self, w):
+        self.agg, self.dims, self.w_self, self.w_neigh = "gc_sum", (w.shape[1], w.shape[0]), [None], [w]
+        self.bias, self.relu, self.w_out, self.b_out, self.gin_eps = [np.zeros(w.shape[0], np.float32)], [False], [], [], 0.0
+
+
+def _ring_transform(x, w):
+    """The transform alone: on a ring every aggregate row is one row of x. The library's output, W times the aggregates in
+    float64, and the magnitudes of each output's terms."""
+    n = x.shape[0]
+    v = np.arange(n, dtype=np.int32)
+    lib = Ripple(n, v, (v + 1) % n)
+    try:
+        lib.init_embeddings(x, _OneLayer(w), transform_first=0)
+        got = lib.get_embeddings(1).astype(np.float64)
+    finally:
+        lib.close()
+    s, w64 = np.roll(x, 1, axis=0).astype(np.float64), w.astype(np.float64)
+    return got, s @ w64.T, np.abs(s) @ np.abs(w64).T
+
+
+# Long row lists at column tiles of 48, 128 and (from 65536 rows) 256.
+LONG_LISTS = [(33001, 48), (33001, 128), (65667, 256)]
+
+
+# A product inside the fp32 range whose operands' first bf16 parts, rounded up, have an infinite one.
+@pytest.mark.parametrize("n,n_out", LONG_LISTS)
+@pytest.mark.parametrize("k", [32, 100])
+def test_long_list_transform_at_the_end_of_the_range(n, n_out, k):
+    _say("range", n, k, n_out)
+    rng = np.random.default_rng(k)
+    x, w = (rng.standard_normal(s).astype(np.float32) for s in ((n, k), (n_out, k)))
+    x[7], w[5] = 0, 0
+    x[7, 3] = w[5, 3] = (2 - 2.0 ** -9) * 2.0 ** 63
+    x[70], w[9] = 0, 0
+    x[70, :2], w[9, :2] = 0.99 * 2.0 ** 67, 2.0 ** 60  # two products in the last binade but one
+    got, want, mag = _ring_transform(x, w)
+    assert 3.3e38 < want[8, 5] < 3.4e38 and 3.3e38 < want[71, 9] < 3.4e38
+    assert np.all(np.abs(got - want) <= (k + 16) * 2.0 ** -24 * mag)
