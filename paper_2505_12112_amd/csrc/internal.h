@@ -549,8 +549,8 @@ struct GemmArgs {
   const int *ddeg;
   const float *W;   // [N][K], zeros in the columns between dprev and dq
   const unsigned short *Wb;  // bf16 transforms: W rounded to bf16 (RN-even) as raw bits, [N][K]
-  // fp32 transforms: the three bf16 parts of W (W = hi + mid + lo, each the remainder
-  // rounded RN-even) as raw bits, [3][N][Kp], zeros past K
+  // fp32 transforms: the three bf16 parts of W scaled by 2^24 (2^24 W = hi + mid + lo,
+  // each the remainder rounded RN-even) as raw bits, [3][N][Kp], zeros past K
   const unsigned short *Ws;
   int Kp;           // K rounded up to a multiple of 32
   int bf16;         // 1: the MFMA takes bf16 operands (rounded RN-even at the gather), fp32 accumulation
@@ -582,7 +582,8 @@ int cleanup_blocks_for(long long cap_ops);
 // gemm_variant(expected_rows, N) names the choice (launches with the same variant
 // and arguments are the same launch).
 void launch_gemm(hipStream_t s, const GemmArgs &a, long long max_rows, long long expected_rows);
-// The three bf16 parts of w [rows][K] into parts [3][rows][split_width(K)].
+// The three bf16 parts of w [rows][K], scaled (GemmArgs::Ws), into parts
+// [3][rows][split_width(K)].
 void launch_split_weights(hipStream_t s, const float *w, int rows, int K, unsigned short *parts);
 int gemm_variant(long long expected_rows, int n_cols);
 

@@ -247,3 +247,17 @@ def test_long_list_transform_at_the_end_of_the_range(n, n_out, k):
     got, want, mag = _ring_transform(x, w)
     assert 3.3e38 < want[8, 5] < 3.4e38 and 3.3e38 < want[71, 9] < 3.4e38
     assert np.all(np.abs(got - want) <= (k + 16) * 2.0 ** -24 * mag)
+
+
+# Operands whose low bf16 parts would be denormals (unscaled, 2^-118 loses the last bits and 2^-128 most of them), on
+# either side, against ones large enough that every result is an ordinary number. The bound is fp32's.
+@pytest.mark.parametrize("n,n_out", LONG_LISTS)
+@pytest.mark.parametrize("x_exp,w_exp", [(-118, 40), (-128, 60), (40, -118), (60, -128), (-146, 90), (0, 0)])
+def test_long_list_transform_of_tiny_operands(n, n_out, x_exp, w_exp):
+    _say("tiny", n, n_out, x_exp, w_exp)
+    rng = np.random.default_rng(n_out)
+    k = 64
+    x = (rng.standard_normal((n, k)) * 2.0 ** x_exp).astype(np.float32)
+    w = (rng.standard_normal((n_out, k)) * 2.0 ** w_exp).astype(np.float32)
+    got, want, mag = _ring_transform(x, w)
+    assert np.all(np.abs(got - want) <= (k + 16) * 2.0 ** -24 * mag)
