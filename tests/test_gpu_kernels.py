@@ -261,3 +261,28 @@ def test_long_list_transform_of_tiny_operands(n, n_out, x_exp, w_exp):
     w = (rng.standard_normal((n_out, k)) * 2.0 ** w_exp).astype(np.float32)
     got, want, mag = _ring_transform(x, w)
     assert np.all(np.abs(got - want) <= (k + 16) * 2.0 ** -24 * mag)
+
+
+def _check_fp32_quality(err, rss, k):
+    """Errors of an fp32 sum of k products, given each output's root sum of squares: a running sum rounded k times is off by
+    0.3 sqrt(k) units of 2^-24 of it (rms; sqrt(k / 6), times 0.72 for the mean place in a binade). A product short of its
+    last bf16 part alone is off by some 30. And no side is favoured: the mean of the row means is within six of its standard
+    errors of zero, over all rows and over even and odd ones (an error on one side adds up over a sink's neighbours)."""
+    e = err / (2.0 ** -24 * np.maximum(rss, 1e-30))
+    rms = np.sqrt(np.mean(e * e))
+    assert rms <= 0.3 * np.sqrt(k), rms
+    rows = e.mean(axis=1)
+    for part in (rows, rows[0::2], rows[1::2]):
+        assert abs(part.mean()) <= 6.0 * part.std() / np.sqrt(part.size), (part.mean(), part.std() / np.sqrt(part.size))
+
+
+# K of one step of 32, two, five and sixteen: the signs of the steps balance, or nearly, or cannot.
+@pytest.mark.parametrize("n,n_out", LONG_LISTS)
+@pytest.mark.parametrize("k", [20, 64, 132, 512])
+def test_long_list_transform_has_the_errors_of_an_fp32_sum(n, n_out, k):
+    _say("errors", n, k, n_out)
+    rng = np.random.default_rng(k)
+    x, w = (rng.standard_normal(s).astype(np.float32) for s in ((n, k), (n_out, k)))
+    got, want, _ = _ring_transform(x, w)
+    rss = np.sqrt(np.roll(x, 1, axis=0).astype(np.float64) ** 2 @ (w.astype(np.float64) ** 2).T)
+    _check_fp32_quality(got - want, rss, k)
