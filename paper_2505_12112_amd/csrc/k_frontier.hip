@@ -1283,8 +1283,13 @@ struct Puller {
   }
 };
 
-// Messages are summed in fp32 (at most a few per group in a row, then across the
-// groups), whole aggregates in fp64.
+// Messages are summed in fp32, at most 256 in a row: by groups of up to 16 lanes, a
+// sink's (1024 among 4 groups or more); by 32 or 64 lanes, those of 64 in-arcs, whose
+// sums are then added up (at most 16); and of a row that a block sums those of 64
+// in-arcs, whose sums are added up in fp64. (With one fp32 sum per group throughout, a
+// hub of 60,000 equal messages was off by 2965 units of 2^-24 of the sum at 256 wide and
+// 556 at 64, and 1024 messages at 256 wide by 144; now 8, 2 and 10.) Whole aggregates are
+// summed in fp64.
 template <bool MSG>
 using PullAcc = typename std::conditional<MSG, float, double>::type;
 
@@ -1380,7 +1385,7 @@ __device__ inline void pull_long(const PullArgs &p, const Puller<MSG> &pl, const
                                  double (*part)[4 * G * NC], int *messages) {
   const int lane = pl.lane, wave = threadIdx.x / kWave;
   const int deg = __builtin_amdgcn_readfirstlane(s.deg);
-  PullAcc<MSG> acc[NC][4] = {};
+  double sum[NC][4] = {};
   int found = 0;
   constexpr int kStep = kPullWaves * kWave;
   int e0 = __builtin_amdgcn_readfirstlane(wave * kWave);
@@ -1393,16 +1398,25 @@ __device__ inline void pull_long(const PullArgs &p, const Puller<MSG> &pl, const
     double coef;
     const int cnt = pl.resolve(a, deg - e0 < kWave ? deg - e0 : kWave, coef);
     found += cnt;
-    pull_rows<G, NC, U, COEF>(p, a.u, coef, cnt, k0, acc);
+    if constexpr (MSG) {
+      float acc[NC][4] = {};
+      pull_rows<G, NC, U, COEF>(p, a.u, coef, cnt, k0, acc);
+#pragma unroll
+      for (int q = 0; q < NC; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum[q][j] += static_cast<double>(acc[q][j]);
+    } else {
+      pull_rows<G, NC, U, COEF>(p, a.u, coef, cnt, k0, sum);
+    }
     if (more > 0) pl.look_up(b);
     a = b;
   }
-  pull_reduce<G, NC>(acc);
+  pull_reduce<G, NC>(sum);
   if (lane < G) {
 #pragma unroll
     for (int q = 0; q < NC; ++q)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) part[wave][k0 + 4 * G * q + j] = acc[q][j];
+      for (int j = 0; j < 4; ++j) part[wave][k0 + 4 * G * q + j] = sum[q][j];
   }
   if (lane == 0) messages[wave] = found;
   __syncthreads();
@@ -1412,10 +1426,10 @@ __device__ inline void pull_long(const PullArgs &p, const Puller<MSG> &pl, const
   if (total > 0) {  // (a long row has arcs: without MSG always)
     float *sv = p.S + static_cast<long long>(s.v) * p.d;
     for (int k = threadIdx.x; k < p.d; k += kPullWaves * kWave) {
-      double sum = MSG ? static_cast<double>(sv[k]) : 0.0;
+      double row = MSG ? static_cast<double>(sv[k]) : 0.0;
 #pragma unroll
-      for (int w = 0; w < kPullWaves; ++w) sum += part[w][k];
-      sv[k] = static_cast<float>(sum);
+      for (int w = 0; w < kPullWaves; ++w) row += part[w][k];
+      sv[k] = static_cast<float>(row);
     }
     if (MSG && p.mark != nullptr && threadIdx.x == 0) mark_only(p.mark, s.v);
   }
@@ -1456,8 +1470,18 @@ __device__ inline void pull_body(const PullArgs &p) {
     const int v = __builtin_amdgcn_readfirstlane(s0.v), deg = __builtin_amdgcn_readfirstlane(s0.deg);
     if (deg <= long_from) {
       PullAcc<MSG> acc[NC][4] = {};
+      // The sink's row, which comes with its first messages; where the sums of 64s are
+      // folded, those first (both at once cost a wave per SIMD) and the row last.
       float4u prev[NC] = {};
+      const bool fold = MSG && G >= 32 && deg > kWave;
       float *sv = p.S + static_cast<long long>(v) * p.d;
+      const auto load_prev = [&] {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          const int k = k0 + 4 * G * q;
+          prev[q] = *reinterpret_cast<const float4u *>(sv + (k < p.d ? k : 0));
+        }
+      };
       bool any = false;
       Arcs a = a0;
       for (int e0 = 0; e0 < deg; e0 += kWave) {
@@ -1466,19 +1490,31 @@ __device__ inline void pull_body(const PullArgs &p) {
         if (more > 0) b = pl.arcs(s0.off + e0 + kWave, more < kWave ? more : kWave);
         double coef;
         const int cnt = pl.resolve(a, deg - e0 < kWave ? deg - e0 : kWave, coef);
-        if (MSG && cnt > 0 && !any) {  // the sink's row comes with its first messages
+        if (MSG && cnt > 0 && !any) {
           any = true;
-#pragma unroll
-          for (int q = 0; q < NC; ++q) {
-            const int k = k0 + 4 * G * q;
-            prev[q] = *reinterpret_cast<const float4u *>(sv + (k < p.d ? k : 0));
-          }
+          if (!fold) load_prev();
         }
         pull_rows<G, NC, U, COEF>(p, a.u, coef, cnt, k0, acc);
+        if (fold) {
+#pragma unroll
+          for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              prev[q][j] += static_cast<float>(acc[q][j]);
+              acc[q][j] = 0;
+            }
+        }
         if (more > 0) pl.look_up(b);
         a = b;
       }
       if (!MSG || any) {
+        if (fold) {
+#pragma unroll
+          for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[q][j] = prev[q][j];
+          load_prev();
+        }
         pull_reduce<G, NC>(acc);
         if (lane < G) pull_store<G, NC, MSG>(sv, p.d, k0, acc, prev);
         if (MSG && p.mark != nullptr && lane == 0) mark_only(p.mark, v);
@@ -1502,8 +1538,11 @@ template <int G, int NC, int U, bool COEF>
 __global__ __launch_bounds__(256) void k_recompute(PullArgs p) {
   pull_body<G, NC, U, false, COEF>(p);
 }
+// (At 65 to 96 and 129 to 192 columns four waves per SIMD fit, by a register or three. A
+// batch of 1000 on 300,000 vertices and 12M arcs with dense layers 80 wide: 658 us, now
+// 584; 160 wide, with its fp64 sums of long rows, 680 and 702; 100 wide 555 and 567.)
 template <int G, int NC, int U, bool COEF>
-__global__ __launch_bounds__(256) void k_pull_msgs(PullArgs p) {
+__global__ __launch_bounds__(256, NC == 3 && !COEF ? 4 : 1) void k_pull_msgs(PullArgs p) {
   pull_body<G, NC, U, true, COEF>(p);
 }
 

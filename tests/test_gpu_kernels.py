@@ -286,3 +286,31 @@ def test_long_list_transform_has_the_errors_of_an_fp32_sum(n, n_out, k):
     got, want, _ = _ring_transform(x, w)
     rss = np.sqrt(np.roll(x, 1, axis=0).astype(np.float64) ** 2 @ (w.astype(np.float64) ** 2).T)
     _check_fp32_quality(got - want, rss, k)
+
+
+# Equal messages, whose fp32 sums are off on one side by up to half a unit of 2^-24 of the sum per addition, into sinks of
+# few and of very many in-arcs. Additions in a row: a group's share of 1024 in-arcs (groups of up to 16 lanes); its share
+# of 64, then 16 such sums (32 and 64 lanes); its share of 64 for rows that a block sums, in fp64 from there. Then the
+# groups (at most 4 levels), the row and the rounding.
+@pytest.mark.parametrize("width,lanes", [(16, 4), (32, 8), (64, 16), (96, 8), (100, 32), (160, 16), (256, 64), (512, 64)])
+@pytest.mark.parametrize("mode", ["pull", "dense"])
+def test_pulled_messages_of_hubs_are_summed_in_blocks(width, lanes, mode):
+    _say("hub sums", width, mode)
+    n, degs = 62000, np.array([60000, 1024, 1025, 500, 64])
+    src = np.concatenate([np.arange(100, 100 + d, dtype=np.int32) for d in degs])
+    dst = np.repeat(np.arange(degs.size, dtype=np.int32), degs)
+    lib = Ripple(n, src, dst)
+    try:
+        lib.init_embeddings(np.zeros((n, width), np.float32), _OneLayer(np.ones((3, width), np.float32)), transform_first=0)
+        lib.set_scatter_mode(mode)
+        ops = np.full((60000, 4), -1, np.int32)
+        ops[:, 0], ops[:, 1], ops[:, 3] = 3, np.arange(100, 60100), np.arange(60000)
+        message = np.float32(1 + 0.9 * 2.0 ** -11)  # sums from 2^13 on round most of its low bits off, always down
+        lib.apply_updates(ops, np.full((60000, width), message, np.float32))
+        got = lib.get_aggregates(1, np.arange(degs.size, dtype=np.int32)).astype(np.float64)
+    finally:
+        lib.close()
+    want = degs[:, None] * np.float64(message)
+    groups = 64 // lanes
+    chain = np.where(degs > 1024, 64 // groups, 64 // groups + 16 if lanes >= 32 else 1024 // groups)
+    assert np.all(np.abs(got - want) <= (chain + 6)[:, None] * 2.0 ** -24 * want)
