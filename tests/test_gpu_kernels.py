@@ -4,6 +4,7 @@ import sys
 import numpy as np
 import pytest
 
+from oracle import ripple_oracle as O
 from paper_2505_12112_amd import synth
 from paper_2505_12112_amd.ripple import Ripple
 from tests.harness import Pair, check_embeddings_conditioned, fp32_forward_bound, random_valid_batch
@@ -111,10 +112,35 @@ def _transform_reference(p, l=1):
     return ref, fp32_forward_bound(p.orc, p.orc.embeddings(), l)
 
 
+def _check_fp32_rms(err, rss, k, more=0.0):
+    """Errors of an fp32 sum of k products, given each output's root sum of squares: a running sum rounded k times is off by
+    0.3 sqrt(k) units of 2^-24 of it (rms; sqrt(k / 6), times 0.72 for the mean place in a binade), and by `more` where the
+    operands themselves are rounded. A sum whose weights lack their last bf16 part is off by 42 at any k (59 if both operands
+    do), one of all nine part products but the three last by 0.1. Returns the errors in units."""
+    e = err / (2.0 ** -24 * np.maximum(rss, 1e-30))
+    rms = np.sqrt(np.mean(e * e))
+    assert rms <= 0.3 * np.sqrt(k) + more, rms
+    return e
+
+
+def _check_transform(p, k, agg):
+    """Layer 1 of a one-layer model against float64: half the forward error bound and, but for GIN's two products and rows
+    shorter than a K step's half, the errors of an fp32 sum over the operand (its scales and sums are rounded: 1 unit)."""
+    want, bound = _transform_reference(p)
+    err = p.lib.get_embeddings(1).astype(np.float64) - want
+    assert np.all(np.abs(err) <= 0.5 * bound[:, None] + 1e-30)
+    if agg == "gin" or k < 16:
+        return
+    m, h = p.orc.model, p.orc.embeddings()[0]
+    rss = O.aggregate(p.orc.graph, h, agg) ** 2 @ (m.w_neigh[0] ** 2).T + m.bias[0] ** 2
+    if m.w_self[0] is not None:
+        rss = rss + h ** 2 @ (m.w_self[0] ** 2).T
+        k *= 2
+    _check_fp32_rms(err, np.sqrt(rss), k, more=1.0)
+
+
 # The transform of long row lists: column tiles of 16, 32, 48, 64 and 128, remainders of the 32-deep K steps and of the
-# 128-row tiles, every operand form. 33,001 rows take the long-list kernel at every width. The bound is half of the fp32
-# forward error bound that the parity tests use: three bf16 parts carry fp32's 24 bits, the part products left out are
-# below 2^-25 of a product, and the sums are fp32.
+# 128-row tiles, every operand form. 33,001 rows take the long-list kernel at every width.
 @pytest.mark.parametrize("k,n_out", [(4, 16), (8, 17), (28, 32), (32, 33), (36, 47), (60, 48), (64, 49), (100, 64),
                                      (96, 65), (128, 128), (132, 130), (256, 256), (20, 3), (1, 5), (3, 47), (5, 33),
                                      (31, 70), (75, 130), (130, 131), (67, 19)])
@@ -124,10 +150,23 @@ def test_long_list_transform_matches_float64(k, n_out, agg, tf):
     rng = np.random.default_rng(k * 1000 + n_out)
     p = _pair(rng, 33001, 66000, (k, n_out), agg, transform_first=tf)
     try:
-        want, bound = _transform_reference(p)
-        err = np.abs(p.lib.get_embeddings(1).astype(np.float64) - want)
-        assert np.all(err <= 0.5 * bound[:, None] + 1e-30)
+        _check_transform(p, k, agg)
         p.step(random_valid_batch(rng, p.orc, 50, k))
+    finally:
+        p.close()
+
+
+# From 65536 rows on, outputs of whole pairs of 128 columns take 256-column tiles: one and a remainder of one, odd widths
+# on either side, K of one step to nine, and with 1024 columns more tiles (2056) than blocks (2048).
+@pytest.mark.parametrize("k,n_out,agg,tf", [(64, 129, "sum", 0), (67, 130, "gcn", 0), (128, 200, "mean", 0), (132, 256, "gc_sum", 0),
+                                            (128, 385, "sum", 0), (257, 256, "gc_mean", 0), (100, 256, "gin", 0), (256, 200, "sum", 1),
+                                            (75, 130, "gcn", 1), (1, 256, "sum", 0), (20, 256, "gcn", 0), (36, 1024, "gc_sum", 0)])
+def test_wide_tile_transform_matches_float64(k, n_out, agg, tf):
+    _say("wide tiles", k, n_out, agg, tf)
+    rng = np.random.default_rng(k * 1000 + n_out)
+    p = _pair(rng, 65667, 130000, (k, n_out), agg, transform_first=tf)
+    try:
+        _check_transform(p, k, agg)
     finally:
         p.close()
 
@@ -153,12 +192,12 @@ def test_short_list_transform_on_odd_widths(n, k, n_out, agg, tf):
 
 
 # Infinities, NaNs and values past bf16's range reach exactly the outputs that fp32 arithmetic gives them.
-@pytest.mark.parametrize("k,n_out", [(32, 128), (100, 47)])
+@pytest.mark.parametrize("k,n_out", [(32, 128), (100, 47), (100, 256)])
 @pytest.mark.parametrize("where", ["features", "weights"])
 def test_long_list_transform_keeps_infinities_and_nans(k, n_out, where):
     _say("non-finite", k, n_out, where)
     rng = np.random.default_rng(k)
-    n = 33001
+    n = 65667 if n_out == 256 else 33001  # 256-column tiles
     src, dst = synth.erdos_renyi(n, 40000, rng)
     x = rng.standard_normal((n, k)).astype(np.float32)
     w = synth.model_weights(synth.ModelSpec("gc_sum", (k, n_out)), rng, bias_std=0.1)
@@ -263,20 +302,9 @@ def test_long_list_transform_of_tiny_operands(n, n_out, x_exp, w_exp):
     assert np.all(np.abs(got - want) <= (k + 16) * 2.0 ** -24 * mag)
 
 
-def _check_fp32_quality(err, rss, k):
-    """Errors of an fp32 sum of k products, given each output's root sum of squares: a running sum rounded k times is off by
-    0.3 sqrt(k) units of 2^-24 of it (rms; sqrt(k / 6), times 0.72 for the mean place in a binade). A product short of its
-    last bf16 part alone is off by some 30. And no side is favoured: the mean of the row means is within six of its standard
-    errors of zero, over all rows and over even and odd ones (an error on one side adds up over a sink's neighbours)."""
-    e = err / (2.0 ** -24 * np.maximum(rss, 1e-30))
-    rms = np.sqrt(np.mean(e * e))
-    assert rms <= 0.3 * np.sqrt(k), rms
-    rows = e.mean(axis=1)
-    for part in (rows, rows[0::2], rows[1::2]):
-        assert abs(part.mean()) <= 6.0 * part.std() / np.sqrt(part.size), (part.mean(), part.std() / np.sqrt(part.size))
-
-
-# K of one step of 32, two, five and sixteen: the signs of the steps balance, or nearly, or cannot.
+# K of one step of 32, two, five and sixteen: the signs of the steps balance, or nearly, or cannot. No side is favoured: the
+# mean of the row means is within six of its standard errors of zero, over all rows and over even and odd ones (an error on
+# one side adds up over a sink's neighbours). Without a bias: adding one constant to every row rounds all of them alike.
 @pytest.mark.parametrize("n,n_out", LONG_LISTS)
 @pytest.mark.parametrize("k", [20, 64, 132, 512])
 def test_long_list_transform_has_the_errors_of_an_fp32_sum(n, n_out, k):
@@ -285,7 +313,9 @@ def test_long_list_transform_has_the_errors_of_an_fp32_sum(n, n_out, k):
     x, w = (rng.standard_normal(s).astype(np.float32) for s in ((n, k), (n_out, k)))
     got, want, _ = _ring_transform(x, w)
     rss = np.sqrt(np.roll(x, 1, axis=0).astype(np.float64) ** 2 @ (w.astype(np.float64) ** 2).T)
-    _check_fp32_quality(got - want, rss, k)
+    rows = _check_fp32_rms(got - want, rss, k).mean(axis=1)
+    for part in (rows, rows[0::2], rows[1::2]):
+        assert abs(part.mean()) <= 6.0 * part.std() / np.sqrt(part.size), (part.mean(), part.std() / np.sqrt(part.size))
 
 
 # Equal messages, whose fp32 sums are off on one side by up to half a unit of 2^-24 of the sum per addition, into sinks of
