@@ -43,6 +43,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 FP32_MFMA_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix
 BF16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix
+SPLIT_MFMA_PEAK_TFLOPS = BF16_MFMA_PEAK_TFLOPS / 6  # fp32 products as six products of bf16 parts
 PROFILED_BATCHES = 60          # untimed batches whose kernels are timed for the roofline
 
 
@@ -189,6 +190,16 @@ def profiled(lib, staged, phases):
     return ph, modes
 
 
+def gemm_unit(p, prec):
+    """Peak of the matrix unit that a phase's transforms run on, and their kernels. fp32 transforms of long row lists (over
+    2 GFLOP a launch; 8192 or 32768 rows by width) take the bf16 matrix cores, short ones the fp32 MFMA."""
+    if prec == "bf16":
+        return BF16_MFMA_PEAK_TFLOPS, "k_gemm_rows / k_gemm (gather + bf16 MFMA + epilogue)"
+    if p["flops"] > 2e9 * p["launches"]:
+        return SPLIT_MFMA_PEAK_TFLOPS, "k_gemm_split (gather + bf16 MFMA on three parts per fp32 operand + epilogue)"
+    return FP32_MFMA_PEAK_TFLOPS, "k_gemm_rows (gather + fp32 MFMA + epilogue)"
+
+
 def roof(p, name, traffic, peak_tflops, gemm_label):
     """Roofline of a phase from its kernel-timed sums: algorithmic work per launch
     over the average kernel duration."""
@@ -199,8 +210,8 @@ def roof(p, name, traffic, peak_tflops, gemm_label):
               "timing": "kernel-only durations (hipExtLaunchKernelGGL start / stop events) of every launch of the "
                         "phase over an untimed profiled pass",
               "traffic": traffic,
-              "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE in separate runs, "
-                              "calibrated on a plain copy); null when the kernels changed since they were taken"}
+              "traffic_unit": "HBM bytes per launch (rocprofv3 L2-to-fabric requests counted at their sizes, reads and writes "
+                              "in separate runs); null when the kernels changed since they were taken"}
     if name == "gemm":
         per = p["flops"] / p["launches"]
         ach = per / avg_s / 1e12
@@ -235,10 +246,7 @@ def scatter_large(args, torch, np):
         wall = time.perf_counter() - t0
         key = f"{args.large_config}_b{bs}"
         r = roof(ph["scatter"], "scatter", read_traffic(key, "scatter"), None, None)
-        g = roof(ph["gemm"], "gemm", read_traffic(key, "gemm"),
-                 BF16_MFMA_PEAK_TFLOPS if args.gemm == "bf16" else FP32_MFMA_PEAK_TFLOPS,
-                 "k_gemm (gather + bf16 MFMA + epilogue)" if args.gemm == "bf16" else
-                 "k_gemm_split (gather + bf16 MFMA on three parts per fp32 operand + epilogue)")
+        g = roof(ph["gemm"], "gemm", read_traffic(key, "gemm"), *gemm_unit(ph["gemm"], args.gemm))
         if r is None:
             return None
         r.update({"workload": args.large_config, "batch": bs, "batches": args.large_batches,
@@ -343,10 +351,8 @@ def main():
     ph, _ = profiled(lib, prof_staged, ("net", "topo", "layer0", "scatter", "compact", "gemm", "other", "total"))
     nb = len(prof_staged)
     key = f"{args.config}_b{bs}"
-    gemm_peak = BF16_MFMA_PEAK_TFLOPS if args.gemm == "bf16" else FP32_MFMA_PEAK_TFLOPS
     r_scatter = roof(ph["scatter"], "scatter", read_traffic(key, "scatter"), None, None)
-    r_gemm = roof(ph["gemm"], "gemm", read_traffic(key, "gemm"), gemm_peak,
-                  f"k_gemm_rows / {'k_gemm' if args.gemm == 'bf16' else 'k_gemm_split'} (gather + MFMA + epilogue)")
+    r_gemm = roof(ph["gemm"], "gemm", read_traffic(key, "gemm"), *gemm_unit(ph["gemm"], args.gemm))
     dominant = "gemm" if ph["gemm"]["ms"] >= ph["scatter"]["ms"] else "scatter"
     roofline = r_gemm if dominant == "gemm" else r_scatter
     other = r_scatter if dominant == "gemm" else r_gemm

@@ -238,14 +238,15 @@ RIPPLE_API ripple_status ripple_get_embeddings(ripple_ctx *ctx, int32_t layer, c
 
 /* ripple_get_embeddings for callers that cannot allocate device memory (code
  * under HIP graph capture, serving loops, harnesses that forbid allocation): the
- * same rows, with the same arguments and errors, staged through a file-scope
- * device array of 32 MiB instead of buffers allocated per call (ripple_get_embeddings
- * allocates two per call with ids and more than 1 MiB of ids and rows; smaller reads of
- * both go through pinned host memory of the context). The ids and gathered rows must fit in it:
+ * same rows, with the same arguments and errors, staged without a buffer allocated
+ * per call. Calls whose ids and rows take at most 1 MiB go through pinned host memory
+ * of the context, as ripple_get_embeddings with ids does; larger ones (for which
+ * ripple_get_embeddings allocates two buffers) through a file-scope device array of
+ * 32 MiB. The ids and gathered rows must fit in that array, whichever way they take:
  * count * 4 bytes (rounded up to 256) + count * d_layer * 4 bytes <= 32 MiB, else
  * RIPPLE_E_INVALID naming the limit. Each GPU the library runs on holds its own
- * copy of the array until the process ends; every call on that GPU, from any
- * context, stages through it, so calls that overlap on one GPU (other threads,
+ * copy of the array until the process ends; every call on that GPU that needs it, from
+ * any context, stages through it, so calls that overlap on one GPU (other threads,
  * other contexts) race and must be serialised by the caller. Allocates nothing:
  * no hipMalloc, hipFree or allocating library routine. */
 RIPPLE_API ripple_status ripple_get_embeddings_static(ripple_ctx *ctx, int32_t layer, const int32_t *ids,

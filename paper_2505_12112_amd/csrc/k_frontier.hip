@@ -803,8 +803,8 @@ __global__ __launch_bounds__(256) void k_scatter(int d, int ld, const int *list,
   }
 }
 
-constexpr int kPullArcs = 4;  // arcs per lane per chunk (the pull and the bucket passes)
-constexpr int kPullChunk = kWave * kPullArcs;
+constexpr int kBinArcs = 4;  // arcs per lane per chunk (the bucket passes)
+constexpr int kBinChunk = kWave * kBinArcs;
 
 // Exclusive prefix sums of a[0, n) in LDS, in place, by a block of kBinThreads
 // threads (each a run of consecutive entries); ends with a barrier.
@@ -838,9 +838,9 @@ __device__ inline void block_exclusive_scan(int *a, int n, int *wave_sums) {
 }
 
 // The bucket form's passes over the pushed arcs (numbered as in the scatter), in
-// chunks of up to kPullChunk consecutive arcs per wave (a contiguous run of chunks
+// chunks of up to kBinChunk consecutive arcs per wave (a contiguous run of chunks
 // per wave, so that a block owns the same arcs in both passes), each lane up to
-// kPullArcs consecutive arcs with all their loads in flight together. The arcs are
+// kBinArcs consecutive arcs with all their loads in flight together. The arcs are
 // sorted by sink in two levels: into bins of 2^shift consecutive sinks here, then
 // by sink within each bin (k_bin_sort). Counting pass (SCATTER false): marks the
 // net arcs' heads and, under a self term, D in bm_x, counts the block's arcs per
@@ -886,7 +886,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_arcs(const int *list, const
   const long long waves = num_waves();
   const long long n1 = nD + 1;  // a compacted list: doff[nD] holds the arc total
   int C = 1;
-  while (C < kPullChunk && static_cast<long long>(C) * waves < E) C <<= 1;
+  while (C < kBinChunk && static_cast<long long>(C) * waves < E) C <<= 1;
   const int per_lane = C > kWave ? C / kWave : 1;
   const long long chunks = (E + C - 1) / C;
   const long long per = (chunks + waves - 1) / waves;
@@ -898,11 +898,11 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_arcs(const int *list, const
     const long long elast = e0 + C - 1 < E - 1 ? e0 + C - 1 : E - 1;
     ja = ja < 0 ? wave_last_le(doff, 0, n1, e0) : owner_from(doff, ja, n1, e0);
     const long long jb = C == 1 ? ja : owner_from(doff, ja, n1, elast);
-    long long e[kPullArcs];
-    int r[kPullArcs];
-    bool on[kPullArcs];
+    long long e[kBinArcs];
+    int r[kBinArcs];
+    bool on[kBinArcs];
 #pragma unroll
-    for (int a = 0; a < kPullArcs; ++a) {
+    for (int a = 0; a < kBinArcs; ++a) {
       e[a] = e0 + static_cast<long long>(lane) * per_lane + a;
       on[a] = a < per_lane && e[a] <= elast;
       r[a] = static_cast<int>(ja);
@@ -911,39 +911,39 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_arcs(const int *list, const
       if (jb - ja < kWave) {
         // the window's offsets, one per lane; every lane takes part in the shuffles
         const long long mine = ja + lane <= jb ? doff[ja + lane] : (1LL << 62);
-        int cnt[kPullArcs] = {};
+        int cnt[kBinArcs] = {};
         for (int t = 0; t <= static_cast<int>(jb - ja); ++t) {
           const long long o = __shfl(mine, t);
 #pragma unroll
-          for (int a = 0; a < kPullArcs; ++a) cnt[a] += o <= e[a] ? 1 : 0;
+          for (int a = 0; a < kBinArcs; ++a) cnt[a] += o <= e[a] ? 1 : 0;
         }
 #pragma unroll
-        for (int a = 0; a < kPullArcs; ++a) r[a] = static_cast<int>(ja) + cnt[a] - 1;
+        for (int a = 0; a < kBinArcs; ++a) r[a] = static_cast<int>(ja) + cnt[a] - 1;
       } else {
 #pragma unroll
-        for (int a = 0; a < kPullArcs; ++a)
+        for (int a = 0; a < kBinArcs; ++a)
           if (on[a]) r[a] = static_cast<int>(upper_bound(doff, ja, jb + 1, e[a]) - 1);
       }
     }
-    long long slot[kPullArcs];
-    int v[kPullArcs];
+    long long slot[kBinArcs];
+    int v[kBinArcs];
 #pragma unroll
-    for (int a = 0; a < kPullArcs; ++a) {
+    for (int a = 0; a < kBinArcs; ++a) {
       const int u = on[a] ? list[r[a]] : 0;
       slot[a] = on[a] ? out.off[u] + (e[a] - doff[r[a]]) : 0;
     }
 #pragma unroll
-    for (int a = 0; a < kPullArcs; ++a) v[a] = on[a] ? out.col[slot[a]] : 0;
+    for (int a = 0; a < kBinArcs; ++a) v[a] = on[a] ? out.col[slot[a]] : 0;
     if (!SCATTER) {
 #pragma unroll
-      for (int a = 0; a < kPullArcs; ++a)
+      for (int a = 0; a < kBinArcs; ++a)
         if (on[a]) atomicAdd(&bins[v[a] >> b.shift], 1);
     } else {
-      float w[kPullArcs];
+      float w[kBinArcs];
 #pragma unroll
-      for (int a = 0; a < kPullArcs; ++a) w[a] = on[a] && b.tw != nullptr ? out.wt[slot[a]] : 1.0f;
+      for (int a = 0; a < kBinArcs; ++a) w[a] = on[a] && b.tw != nullptr ? out.wt[slot[a]] : 1.0f;
 #pragma unroll
-      for (int a = 0; a < kPullArcs; ++a) {
+      for (int a = 0; a < kBinArcs; ++a) {
         if (!on[a]) continue;
         const int p = atomicAdd(&bins[v[a] >> b.shift], 1);
         b.tv[p] = v[a];

@@ -791,8 +791,10 @@ void add_launches(ripple_ctx *c, int phase, int k) {
 //              layer at batch 1000, stress's first and dense_large's second at
 //              batch 100); it is taken only when its estimate is a quarter below
 //              every other form's.
-// (The pull, dense and recompute rates are of those forms' earlier kernels, up to a
-// fifth slower than today's; they choose the same forms on the traced workloads.)
+// The pull, dense and recompute rates have not been fitted again to today's kernels,
+// which flush a row with one plain read and write instead of atomics, list no vertices
+// for a dense layer and are up to a fifth faster. On the traced workloads the same forms
+// are the fastest; near a crossover push and bucket are favoured.
 // Every reanchor_every-th batch recomputes every layer (the drift budget), whatever
 // the form.
 enum LayerMode { kPushLayer = 0, kPullLayer = 1, kDenseLayer = 2, kRecomputeLayer = 3, kBucketLayer = 4 };
