@@ -191,11 +191,12 @@ def profiled(lib, staged, phases):
 
 
 def gemm_unit(p, prec):
-    """Peak of the matrix unit that a phase's transforms run on, and their kernels. fp32 transforms of long row lists (over
-    2 GFLOP a launch; 8192 or 32768 rows by width) take the bf16 matrix cores, short ones the fp32 MFMA."""
+    """Peak of the matrix unit that most of a phase's transform work runs on, and the kernel. fp32 transforms of long row
+    lists (8192 or 32768 rows on, by width: averages over 1 GFLOP a launch) take the bf16 matrix cores, short ones the
+    fp32 MFMA."""
     if prec == "bf16":
         return BF16_MFMA_PEAK_TFLOPS, "k_gemm_rows / k_gemm (gather + bf16 MFMA + epilogue)"
-    if p["flops"] > 2e9 * p["launches"]:
+    if p["flops"] > 1e9 * p["launches"]:
         return SPLIT_MFMA_PEAK_TFLOPS, "k_gemm_split (gather + bf16 MFMA on three parts per fp32 operand + epilogue)"
     return FP32_MFMA_PEAK_TFLOPS, "k_gemm_rows (gather + fp32 MFMA + epilogue)"
 
