@@ -1222,13 +1222,14 @@ typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 // (or out-degrees), the arcs of the one after, the row bounds of the third and the id
 // of the fourth are in flight. Sinks of more than long_from in-arcs go to k_pull_long.
 // Bound by the row reads that leave the L2s, 128 bytes at a time (a 47-wide row, 192
-// bytes, costs 256; 5.9 TB/s of them on dense_large's third layer). The message pull
+// bytes, costs 256; 6.2 TB/s of them on dense_large's third layer). The message pull
 // there took 3.83 ms at batch 100 and 4.85 at batch 1000 when its lane groups loaded 4
 // bytes per lane, walked windows of 64 arcs with the non-member arcs in place, and
-// flushed with atomics; now 3.15 and 4.4; on the 3-layer mean workload at batch 1000
-// (256 wide) 73 us, now 59; RMAT 2^20 at batch 2500 (64 wide) 1.05 ms, now 0.92; the
+// flushed with atomics; now 3.1 and 4.5; on the 3-layer mean workload at batch 1000
+// (256 wide) 73 us, now 59; RMAT 2^20 at batch 2500 (64 wide) 1.05 ms, now 0.92; but RMAT
+// 2^23 at batch 10000, where most sinks have few in-arcs, 8.7 ms and now 9.1; the
 // bootstrap of dense_large 60, 30 and 15.6 ms for rows 256, 100 and 47 wide with one
-// load of 4 bytes per lane in flight per wave, now 18.8, 8.9 and 5.4. Non-temporal row
+// load of 4 bytes per lane in flight per wave, now 18.2, 8.8 and 5.2. Non-temporal row
 // loads took the batch 100 pull from 2.4 to 3.9 ms (its short rows).
 struct Sink {
   int v, deg;  // v < 0: none
